@@ -56,16 +56,17 @@ struct StageArgs {
 // inside it the least in magnitude of 3 N, 5/6 N + A/3 and A, since f is concave there;
 // so the limiter is two minima of magnitudes and needs no division and no branch (the
 // upwind side and the branch differ from lane to lane).
+// Where a comparison of r is undefined (a NaN, an infinity) the value is C where A = 0 (a
+// NaN of C stays one) or where a NaN of A leaves N >= 0, else D, as the chain of branches
+// gives it: N's sign is selected by A > 0, the last minimum is a selection of D.
 __device__ inline double cui_flux(double a, double r0, double r1, double r2, double r3) {
     const bool up = a > 0.0;
     const double U = up ? r0 : r3, C = up ? r1 : r2, D = up ? r2 : r1;
     const double A = D - U, N = C - U, An = fabs(A);
-    const double Nn = __builtin_bit_cast(double, __builtin_bit_cast(long long, N) ^
-                                                     (__builtin_bit_cast(long long, A) & (1LL << 63)));   // N sign(A)
-    const double w1 = fmin(3.0 * Nn, __builtin_fma(5.0 / 6.0, Nn, An * (1.0 / 3.0)));
-    const double w = w1 < An ? w1 : An;                   // (fmin would drop a NaN of A)
-    const double v = U + copysign(w, A);
-    return a * (Nn <= 0.0 || Nn >= An ? C : v);           // r <= 0, r >= 1 or D = U: upwind
+    const double Nn = A > 0.0 ? N : -N;                   // N sign(A)
+    const double w = fmin(3.0 * Nn, __builtin_fma(5.0 / 6.0, Nn, An * (1.0 / 3.0)));
+    const double v = w < An ? U + copysign(w, A) : D;
+    return a * (Nn <= 0.0 || Nn >= An || A == 0.0 ? C : v);          // r <= 0, r >= 1 or D = U: upwind
 }
 
 // Index of entry m along an axis (mirrored beyond a wall: about the wall face along the

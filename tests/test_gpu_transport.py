@@ -142,3 +142,41 @@ def test_rk3_tile_edges_match_oracle(n):
     stages = _random_stages(dim, n, 7)
     dt = 0.05 * h[0] / max(float(np.abs(a).max()) for st in stages for a in st)
     _check(_gpu(dim, n, h, dt, rho, stages), OT.ssp_rk3(dim, h, dt, rho, stages), dim)
+
+
+def _cui_by_branches(U, C, D):
+    """The limiter as its chain of branches, whose comparisons also decide for NaN and infinities."""
+    with np.errstate(invalid="ignore"):
+        A, N = D - U, C - U
+        An, Nn = np.abs(A), np.where(A > 0.0, N, -N)
+        return np.select([A == 0.0, (Nn <= 0.0) | (Nn >= An), 13.0 * Nn <= 2.0 * An, 5.0 * Nn <= 4.0 * An],
+                         [C, C, U + 3.0 * N, U + (5.0 / 6.0) * N + A / 3.0], D)
+
+
+@pytest.mark.parametrize("n", [(24, 18, 1), (9, 7, 6), (64, 64, 40)], ids=lambda n: "x".join(map(str, n)))
+def test_rk3_carries_nan_and_infinities(n, monkeypatch):
+    """Invalid densities reach the same faces as through the limiter's branches: a NaN in a region
+    of equal densities spreads to the faces downstream of it.  Half of the grid holds one density,
+    the other half random ones; finite results within the module's bound."""
+    dim = 2 if n[2] == 1 else 3
+    h = (1.0 / 64,) * 3
+    rng = np.random.default_rng(5)
+    rho = []
+    for c in range(dim):
+        r = rng.uniform(1.0, 1000.0, W.face_shape(n, c))
+        r[:, :n[1] // 2] = 700.0
+        at = rng.choice(r.size, 12, replace=False)
+        r.reshape(-1)[at] = [np.nan] * 8 + [np.inf] * 4
+        rho.append(r)
+    stages = _random_stages(dim, n, 7)
+    dt = 0.05 * h[0] / max(float(np.abs(a).max()) for st in stages for a in st)
+    monkeypatch.setattr(OT, "cui_face", _cui_by_branches)
+    with np.errstate(invalid="ignore"):
+        want = OT.ssp_rk3(dim, h, dt, rho, stages)
+    got = _gpu(dim, n, h, dt, rho, stages)
+    for c in range(dim):
+        fin = np.isfinite(want[c])
+        assert 0 < np.isnan(want[c]).sum() < want[c].size // 2
+        assert np.array_equal(np.isnan(got[c]), np.isnan(want[c])), c
+        assert np.array_equal(got[c][np.isinf(want[c])], want[c][np.isinf(want[c])]), c
+        assert np.abs(got[c][fin] - want[c][fin]).max() <= 1e-13 * 1000.0
