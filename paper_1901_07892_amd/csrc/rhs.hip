@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(kZX *kZY) k_explicit_rhs3_z(RhsArgs a, int gx,
     const unsigned G = gridDim.x, b = blockIdx.x, per = G >> 3, rest = G & 7, xcd = b & 7, loc = b >> 3;
     const unsigned t = xcd < rest ? xcd * (per + 1) + loc : rest * (per + 1) + (xcd - rest) * per + loc;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int tid = threadIdx.x, tx = tid % kZX, ty = tid / kZX;
+    const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + kZX * ty;
     const int i = (int)(t % gx) * kOX + tx - 1, j = (int)(t / gx % gy) * kOY + ty - 1;
     const int k0 = (int)(t / gx / gy) * kc, k1 = min(k0 + kc, nz);
     const bool out = tx >= 1 && tx <= kOX && ty >= 1 && ty <= kOY && i < nx && j < ny;
@@ -303,7 +303,9 @@ extern "C" stokes_status stokes_explicit_rhs(const stokes_grid *grid, const doub
         int kc = a.nz;
         while (kc > 4 && (double)gx * gy * ((a.nz + kc - 1) / kc) < kRhsBlocks) kc = (kc + 1) / 2;
         const unsigned blocks = (unsigned)gx * (unsigned)gy * (unsigned)((a.nz + kc - 1) / kc);
-        k_explicit_rhs3_z<<<blocks, kZX * kZY, 0, s>>>(a, gx, gy, kc, f[0], f[1], f[2]);
+        // (a launch holds fewer than 2^32 threads along an axis, and the runtime takes more without
+        // an error: blocks of 32 x 8, since a thin grid can have 4e7 of them)
+        k_explicit_rhs3_z<<<blocks, dim3(kZX, kZY), 0, s>>>(a, gx, gy, kc, f[0], f[1], f[2]);
     } else {
         const unsigned blocks = (unsigned)((pts + kRhsBlock - 1) / kRhsBlock);
         k_explicit_rhs2<<<blocks, kRhsBlock, 0, s>>>(a, f[0], f[1]);

@@ -114,3 +114,27 @@ def test_explicit_rhs_tile_edges_match_oracle(n):
     want = A.explicit_rhs(A.OGrid(3, n, h), rho, mu, 1e3, 0.5, clean, rf, (0.4, -9.81, 2.0))
     for c in range(3):
         assert np.abs(got[c] - want[c]).max() <= 1e-12 * np.abs(want[c]).max()
+
+
+def test_explicit_rhs_on_a_grid_of_more_blocks_than_2_to_24():
+    """2 x 101 000 000 x 2 cells: the tiles of such a grid are more than 2^32 threads in a row.
+    All inputs are ones, so every row away from the ends holds the values of a short grid's."""
+    import torch
+    import paper_1901_07892_amd as S
+    h, g = (0.25, 0.5, 0.2), (0.0, 0.0, -9.81)
+
+    def run(ny):
+        grid = S._binding.make_grid(3, (2, ny, 2), h)
+        one = torch.ones(6 * ny + 4, dtype=torch.float64, device="cuda")
+        f = [torch.full(s, np.nan, dtype=torch.float64, device="cuda") for s in ((2, ny, 3), (2, ny + 1, 2), (3, ny, 2))]
+        S.stokes_explicit_rhs(grid, [one] * 3, one, 0.1, 0.5, [one] * 3, f, [one] * 3, g)
+        torch.cuda.synchronize()
+        return f
+    ny = 101_000_000
+    if torch.cuda.mem_get_info()[0] < 10 ** 11:
+        pytest.skip("needs 20 GB of device memory")
+    print("explicit rhs 2x%dx2" % ny, flush=True)
+    small, big = run(32), run(ny)
+    for a, b in zip(small, big):
+        assert torch.equal(a[:, :8], b[:, :8]) and torch.equal(a[:, -8:], b[:, -8:])
+        assert bool((b[:, 8:-8] == a[:, 16:17]).all())
