@@ -18,10 +18,10 @@
 //   - wall-normal faces are not transported and hold rho_n in every stage.
 //
 // GPU mapping: one launch per stage in the caller's C-order layouts: a z-marching kernel
-// that advances the three faces of each cell together (k_rk3_stage3) on 3D grids of at
-// least 2^17 cells, one thread per face (k_rk3_stage) otherwise.  Every control-volume
-// face flux is the same expression for both faces that share it, so the update is
-// exactly conservative in the same sense as its definition.
+// that advances the three faces of each cell together (k_rk3_stage3) on large 3D grids, one
+// thread per face otherwise (2D grids that fill them in tiles, k_rk3_stage2, else in rows,
+// k_rk3_stage).  Every control-volume face flux is the same expression for both faces that
+// share it, so the update is exactly conservative in the same sense as its definition.
 #include "../../include/stokes.h"
 
 #include <hip/hip_runtime.h>
@@ -33,9 +33,14 @@
 namespace {
 
 constexpr int kTrX = 64, kTrY = 4;           // cells (2D: faces) per block
-// The marching kernel from 2^17 cells: 42 us per update at 64^3 against 63 with one
-// thread per face; at 48^3 its few columns are the slower form, 31 against 27.
-constexpr double kTrMarch = 131072;
+// 3D grids march from 3 * 2^17 cells on where their tiles are at least 5/8 full (us per update,
+// marching against a thread per face): 96^3 89 / 107, 128x128x24 48 / 52, 300x40x40 58 / 75,
+// 24x200x200 (3/4 full) 111 / 119; but 64^3 41 / 35, 70^3 56 / 52, 65x65x1000 (0.61 full)
+// 590 / 536, 16x300x300 (half full) 226 / 174, 2x2x500000 5900 / 310.
+constexpr double kTrMarch = 393216, kTrMarchFill = 0.625;
+// 2D grids take tiles that are at least 3/4 full (tiles against rows): 1500^2 112 / 159,
+// 100000x8 46 / 63; but 33x20000 (half full) 63 / 41, 8x100000 253 / 46.
+constexpr double kTrTileFill = 0.75;
 constexpr int kTrBlocks = 4096;              // blocks that a marching launch aims at
 
 struct TrGrid {
@@ -130,15 +135,26 @@ __device__ inline void stage_face(const TrGrid &g, const StageArgs &s, int i, in
     s.out[C][t] = s.a_n * rn + s.a_s * r2 - s.c_dt * R;
 }
 
-// One thread per face: tiles of 64 x 4 faces of one component (blockIdx.y) on one plane,
-// x fastest, then y and z; a block takes every gridDim.x-th tile.
+// One thread per face, the faces of a component (blockIdx.y) numbered in a row: every thread
+// has work whatever the grid's proportions.
 template <int DIM>
-__global__ void __launch_bounds__(kTrX *kTrY) k_rk3_stage(TrGrid g, StageArgs s, int gx, int gy, unsigned tiles) {
+__global__ void __launch_bounds__(kTrX *kTrY) k_rk3_stage(TrGrid g, StageArgs s) {
+    const unsigned t = blockIdx.x * (kTrX * kTrY) + threadIdx.x;
+    const unsigned E0 = g.n[0] + (blockIdx.y == 0), E1 = g.n[1] + (blockIdx.y == 1);
+    const unsigned row = t / E0, k = row / E1;
+    const int i = (int)(t - row * E0), j = (int)(row - k * E1);
+    if (blockIdx.y == 0) stage_face<DIM, 0>(g, s, i, j, (int)k);
+    else if (blockIdx.y == 1) stage_face<DIM, 1>(g, s, i, j, (int)k);
+    else if constexpr (DIM == 3) stage_face<DIM, 2>(g, s, i, j, (int)k);
+}
+
+// 2D in tiles of 64 x 4 faces, x fastest, a block taking every gridDim.x-th tile: the rows
+// above and below a face are read by the same block.
+__global__ void __launch_bounds__(kTrX *kTrY) k_rk3_stage2(TrGrid g, StageArgs s, int gx, unsigned tiles) {
     for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
-        const int i = (int)(t % gx) * kTrX + threadIdx.x, j = (int)(t / gx % gy) * kTrY + threadIdx.y, k = (int)(t / gx / gy);
-        if (blockIdx.y == 0) stage_face<DIM, 0>(g, s, i, j, k);
-        else if (blockIdx.y == 1) stage_face<DIM, 1>(g, s, i, j, k);
-        else if constexpr (DIM == 3) stage_face<DIM, 2>(g, s, i, j, k);
+        const int i = (int)(t % gx) * kTrX + threadIdx.x, j = (int)(t / gx) * kTrY + threadIdx.y;
+        if (blockIdx.y == 0) stage_face<2, 0>(g, s, i, j, 0);
+        else stage_face<2, 1>(g, s, i, j, 0);
     }
 }
 
@@ -320,20 +336,27 @@ extern "C" stokes_status stokes_density_rk3(const stokes_grid *grid, double dt, 
         }
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // the marching kernel takes z chunks of at least 4 planes (a chunk reads four more
-    // planes of density and one of velocity), enough of them for kTrBlocks blocks
-    const bool march = dim == 3 && (double)g.n[0] * g.n[1] * g.n[2] >= kTrMarch;
+    // share of the threads of tiles of tx x ty cells (2D: faces) that have one
+    const int past = dim == 3 ? 0 : 1;
+    auto fill = [&](int tx, int ty) {
+        const double x = g.n[0] + past, y = g.n[1] + past;
+        return x * y / (std::ceil(x / tx) * tx * std::ceil(y / ty) * ty);
+    };
     // tiles of 64 x 4 cells, or 32 x 8 where those leave fewer threads idle
-    auto padded = [&](int tx, int ty) { return (double)((g.n[0] + tx - 1) / tx * tx) * ((g.n[1] + ty - 1) / ty * ty); };
-    const bool narrow = march && padded(kTrX / 2, 2 * kTrY) < padded(kTrX, kTrY);
+    const bool narrow = dim == 3 && fill(kTrX / 2, 2 * kTrY) > fill(kTrX, kTrY);
     const int tx = narrow ? kTrX / 2 : kTrX, ty = narrow ? 2 * kTrY : kTrY;
-    const int past = march ? 0 : 1;              // one thread per face: the faces n along an axis too
+    const bool march = dim == 3 && (double)g.n[0] * g.n[1] * g.n[2] >= kTrMarch && fill(tx, ty) >= kTrMarchFill;
+    const bool tiled = dim == 2 && fill(tx, ty) >= kTrTileFill;
     const int gx = (g.n[0] + past + tx - 1) / tx, gy = (g.n[1] + past + ty - 1) / ty;
+    // z chunks of a marching block: halved down to 3 or 4 planes (a chunk reads four more planes of
+    // density and one of velocity) while there are fewer than kTrBlocks blocks
     int kc = g.n[2];
     while (kc > 4 && (double)gx * gy * ((g.n[2] + kc - 1) / kc) < kTrBlocks) kc = (kc + 1) / 2;
-    const int gz = march ? (g.n[2] + kc - 1) / kc : dim == 3 ? g.n[2] + 1 : 1;
-    // fewer than 2^31 faces per component, each axis of at least 2: at most 2^30 tiles
-    const unsigned tiles = (unsigned)gx * (unsigned)gy * (unsigned)gz, blocks = march ? tiles : std::min(tiles, 1u << 25);
+    const unsigned tiles = (unsigned)gx * (unsigned)gy;
+    // one thread per face of the largest component array, fewer than 2^31
+    size_t most = 0;
+    for (int c = 0; c < dim; ++c) most = std::max(most, face_count(grid, c));
+    const unsigned rows = (unsigned)((most + kTrX * kTrY - 1) / (kTrX * kTrY));
     auto stage = [&](double a_n, double a_s, double c_dt, const double *const rs[3], int st, double *const out[3]) {
         StageArgs a{};
         a.a_n = a_n;
@@ -345,12 +368,13 @@ extern "C" stokes_status stokes_density_rk3(const stokes_grid *grid, double dt, 
             a.u[c] = c < dim ? u_stage[3 * st + c] : nullptr;
             a.out[c] = c < dim ? out[c] : nullptr;
         }
-
-        const dim3 tile(tx, ty);
-        if (narrow) k_rk3_stage3<kTrX / 2><<<blocks, tile, 0, s>>>(g, a, gx, gy, kc);
-        else if (march) k_rk3_stage3<kTrX><<<blocks, tile, 0, s>>>(g, a, gx, gy, kc);
-        else if (dim == 3) k_rk3_stage<3><<<dim3(blocks, 3), tile, 0, s>>>(g, a, gx, gy, tiles);
-        else k_rk3_stage<2><<<dim3(blocks, 2), tile, 0, s>>>(g, a, gx, gy, tiles);
+        const dim3 tile(tx, ty), face(rows, dim);
+        const unsigned chunks = tiles * (unsigned)((g.n[2] + kc - 1) / kc);
+        if (march && narrow) k_rk3_stage3<kTrX / 2><<<chunks, tile, 0, s>>>(g, a, gx, gy, kc);
+        else if (march) k_rk3_stage3<kTrX><<<chunks, tile, 0, s>>>(g, a, gx, gy, kc);
+        else if (tiled) k_rk3_stage2<<<dim3(std::min(tiles, 1u << 25), 2), tile, 0, s>>>(g, a, gx, tiles);
+        else if (dim == 3) k_rk3_stage<3><<<face, kTrX * kTrY, 0, s>>>(g, a);
+        else k_rk3_stage<2><<<face, kTrX * kTrY, 0, s>>>(g, a);
     };
     stage(0.0, 1.0, dt, rho_n, 0, rho_out);
     stage(0.75, 0.25, 0.25 * dt, rho_out, 1, r2);

@@ -153,7 +153,7 @@ def _cui_by_branches(U, C, D):
                          [C, C, U + 3.0 * N, U + (5.0 / 6.0) * N + A / 3.0], D)
 
 
-@pytest.mark.parametrize("n", [(24, 18, 1), (9, 7, 6), (64, 64, 40)], ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("n", [(24, 18, 1), (9, 7, 6), (64, 64, 40), (96, 64, 64), (254, 130, 1)], ids=lambda n: "x".join(map(str, n)))
 def test_rk3_carries_nan_and_infinities(n, monkeypatch):
     """Invalid densities reach the same faces as through the limiter's branches: a NaN in a region
     of equal densities spreads to the faces downstream of it.  Half of the grid holds one density,
@@ -180,3 +180,49 @@ def test_rk3_carries_nan_and_infinities(n, monkeypatch):
         assert np.array_equal(np.isnan(got[c]), np.isnan(want[c])), c
         assert np.array_equal(got[c][np.isinf(want[c])], want[c][np.isinf(want[c])]), c
         assert np.abs(got[c][fin] - want[c][fin]).max() <= 1e-13 * 1000.0
+
+
+@pytest.mark.parametrize("n", [(128, 64, 48), (129, 61, 51), (90, 67, 66), (44, 100, 91), (1024, 200, 2), (65, 65, 94), (255, 6, 1),
+                               (255, 3, 1), (63, 3, 1), (64, 3, 1), (9, 70, 1)], ids=lambda n: "x".join(map(str, n)))
+def test_rk3_routes_match_oracle(n):
+    """Both sides of the rules that choose the kernel: 3D grids of 3 * 2^17 cells and more with 64 x 4
+    tiles, 32 x 8 tiles, one cell past a tile, a shorter last z chunk and columns of 2 cells, and one
+    whose tiles are too empty; 2D grids with full, half empty and nearly empty tiles.  The inputs of
+    the test of the tile edges."""
+    dim = 2 if n[2] == 1 else 3
+    h = (1.0 / 64,) * 3
+    rng = np.random.default_rng(n[0])
+    rho = [10.0 ** rng.uniform(0.0, 3.0, W.face_shape(n, c)) for c in range(dim)]
+    stages = _random_stages(dim, n, 7)
+    dt = 0.05 * h[0] / max(float(np.abs(a).max()) for st in stages for a in st)
+    _check(_gpu(dim, n, h, dt, rho, stages), OT.ssp_rk3(dim, h, dt, rho, stages), dim)
+
+
+@pytest.mark.parametrize("n,like", [((2, 2, 33000), (64, 64, 32)), ((4, 4, 5000), (50, 50, 32)), ((4, 200, 200), (64, 64, 39)),
+                                    ((8, 100000, 1), (900, 900, 1))],
+                         ids=lambda n: "x".join(map(str, n)))
+def test_rk3_narrow_grids_cost_what_their_faces_do(n, like):
+    """Grids a few cells wide take no tiles that leave most threads idle: at most four times
+    as long as a grid of other proportions with as many cells (launches in both)."""
+    import torch
+    import paper_1901_07892_amd as S
+
+    def us(m):
+        dim = 2 if m[2] == 1 else 3
+        grid = S._binding.make_grid(dim, m, (1.0 / 64,) * 3)
+        mk = lambda v: [torch.full(W.face_shape(m, c), v, dtype=torch.float64, device="cuda") for c in range(dim)]
+        rho, u, out = mk(2.0), [mk(0.1) for _ in range(3)], mk(0.0)
+        ws = torch.empty(S.stokes_density_workspace_size(grid), dtype=torch.uint8, device="cuda")
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                S.stokes_density_rk3(grid, 1e-4, rho, u, out, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100.0)
+        return best
+    t, ref = us(n), us(like)
+    print("  density %s %.1f us, %s %.1f us" % (n, t, like, ref), flush=True)
+    assert t <= 4.0 * ref
