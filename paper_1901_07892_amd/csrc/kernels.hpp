@@ -927,8 +927,9 @@ __global__ void __launch_bounds__(1024) k_dense_solve(int n, const R *__restrict
 // right-hand side (the two coarse cycles of a W-cycle, or all cycles of a grid that
 // fits as a whole) are one launch.
 //
-// Two kernels: k_p_small_cycle for levels with walls on every side whose first level
-// has at most 4 cells per thread and colour, k_p_small_general for the others.
+// Two kernels: k_p_small_cycle for levels with walls on every side whose first level it can
+// keep in registers (two or four cells per thread and colour), k_p_small_general for periodic
+// axes and for a few cells more in FP64 in 3D (small_limit has both rules and their measurements).
 enum { SOP_GS = 0, SOP_RESIDUAL = 1, SOP_AVERAGE = 2, SOP_PROLONG = 3, SOP_DENSE = 4, SOP_ZERO = 5 };
 constexpr int kSmallMaxLev = 8;
 constexpr int kSmallThreads = 1024;

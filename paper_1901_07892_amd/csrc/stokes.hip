@@ -621,20 +621,37 @@ void p_level_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, 
     }
 }
 
-// The single-workgroup kernel for the first small level b: cells kept per thread and
-// colour, as few as hold the level.  Four cells of an FP64 3D level (six weights,
-// right-hand side) would need more than the 128 registers of a 1024-thread block.
+// Cells of either colour that the first level of a single-workgroup cycle may have: more
+// leave it to a launch per pass or tile and start the cycle at a coarser level, if there is one.
+// Walls: the register-resident kernel takes four cells a thread in 2D (442x66, its coarsest level
+// of 3663 a colour: 5.3 ms a step against 9.4 pass by pass) and in FP32 (24x20x20 and up, of 4800,
+// are faster from their second level), two in FP64 in 3D.  Between those and 2304 the general
+// kernel (solves, us: 16x16x17, of 2176, 4670 against 4900 in tiles; 18x16x16, of 2304, 2040 / 2065;
+// but 20x16x16, of 2560, 950 / 900, and 19^3, of 3610, 8200 / 6250).
+// Periodic axes: the general kernel up to three cells a thread (40x32x32, second level of 2560:
+// 1630 us against 1705; 128x45, of 2880: 17.9 ms / 18.7; but 20^3 in FP32, of 4000, 1320 / 1200).
+template <int DIM, class R>
+constexpr int small_limit(bool periodic) {
+    return periodic ? 3 * kSmallThreads : DIM == 2 || sizeof(R) == 4 ? 4 * kSmallThreads : 2304;
+}
+inline int half_cells(const Box &b) { return ((b.nx + 1) / 2) * b.ny * b.nz; }
+// k_p_small_general runs the cycle whose first level is b
+template <int DIM, class R>
+bool small_general(const Box &b) {
+    return any_periodic(b) || (DIM == 3 && sizeof(R) == 8 && half_cells(b) > 2 * kSmallThreads);
+}
+
+// The single-workgroup kernel for the first small level: cells kept per thread and colour, as
+// few as hold the level.  (Four cells of an FP64 level need more than the 128 registers of a
+// 1024-thread block: in 2D, with four weights, 29 to 39 of them spill.)
 template <int DIM, class R>
 auto small_kernel(const SmallMG<R> &s) {
     const Box &b = s.b[0];
     const bool relax = s.omega != R(1);
     if (any_periodic(b)) return &k_p_small_general<DIM, R, true>;
-    const int half = ((b.nx + 1) / 2) * b.ny * b.nz;
-    if (half <= 2 * kSmallThreads) return relax ? &k_p_small_cycle<DIM, R, 2, true> : &k_p_small_cycle<DIM, R, 2, false>;
-    if constexpr (DIM == 2 || sizeof(R) == 4) {
-        if (half <= 4 * kSmallThreads) return relax ? &k_p_small_cycle<DIM, R, 4, true> : &k_p_small_cycle<DIM, R, 4, false>;
-    }
-    return &k_p_small_general<DIM, R, false>;
+    if (half_cells(b) <= 2 * kSmallThreads) return relax ? &k_p_small_cycle<DIM, R, 2, true> : &k_p_small_cycle<DIM, R, 2, false>;
+    if constexpr (DIM == 2 || sizeof(R) == 4) return relax ? &k_p_small_cycle<DIM, R, 4, true> : &k_p_small_cycle<DIM, R, 4, false>;
+    else return &k_p_small_general<DIM, R, false>;
 }
 
 // `reps` cycles in a row on the same right-hand side from the first small level down
@@ -1171,7 +1188,7 @@ template <class R>
 void gen_small_ops(const stokes_ctx &c, const MG<R> &mg, int l0, int l, int zg, std::vector<int> &ops) {
     const int rel = l - l0;
     const Box &b = mg.L[l].b;
-    auto half_of = [&](int lev) { const Box &x = mg.L[lev].b; return ((x.nx + 1) / 2) * x.ny * x.nz; };
+    auto half_of = [&](int lev) { return half_cells(mg.L[lev].b); };
     // owner threads of level lev (small_owned): the first wavefront, or none
     auto owners = [&](int lev, int &first) {
         int taken = 0;
@@ -1191,7 +1208,8 @@ void gen_small_ops(const stokes_ctx &c, const MG<R> &mg, int l0, int l, int zg, 
     };
     const int cells = b.nx * b.ny * b.nz;
     auto sweeps = [&](int n, int z) {
-        for (int s = 0; s < n; ++s)
+        // (a list that is too long already is not used: plan_small)
+        for (int s = 0; s < n && ops.size() <= (size_t)(kSmallTab + kSmallMaxOps); ++s)
             for (int colour = 0; colour < 2; ++colour)
                 push(SOP_GS, rel, l, colour, (s == 0 && colour == 0) ? z : 0, half_of(l));
     };
@@ -1216,12 +1234,8 @@ void gen_small_ops(const stokes_ctx &c, const MG<R> &mg, int l0, int l, int zg, 
     sweeps(p_nu_post(c, l), 0);
 }
 
-// Picks the finest level from which the whole cycle fits in the LDS of one
-// workgroup, lays out that LDS and uploads the pass list.  2D: at most 8192 cells
-// there (four per thread and colour): a colour pass over 7293 cells takes one
-// workgroup 1.4 us, a launch of its own 3.2 us.
-constexpr int kSmallMaxCells2 = 8 * kSmallThreads;
-
+// Picks the finest level of at most small_limit cells a colour from which the whole cycle
+// fits in the LDS of one workgroup, lays out that LDS and uploads the pass list.
 template <int DIM, class R>
 void plan_small(stokes_ctx &c, MG<R> &mg) {
     mg.small_l0 = -1;
@@ -1234,8 +1248,9 @@ void plan_small(stokes_ctx &c, MG<R> &mg) {
     for (int l0 = 0; l0 <= mg.nlev - 1; ++l0) {
         const Box &f = mg.L[l0].b;
         if (mg.nlev - l0 > kSmallMaxLev) continue;
-        if ((double)f.nx * f.ny * f.nz > (DIM == 2 ? (double)kSmallMaxCells2 : (double)(1 << 18))) continue;
+        if ((double)((f.nx + 1) / 2) * f.ny * f.nz > small_limit<DIM, R>(any_periodic(f))) continue;
         if (l0 == mg.nlev - 1 && mg.use_dense) break;       // the dense solve alone has a kernel of its own
+        const bool general = small_general<DIM, R>(f);
         SmallMG<R> s{};
         s.nl = mg.nlev - l0;
         size_t off = 0;
@@ -1265,7 +1280,7 @@ void plan_small(stokes_ctx &c, MG<R> &mg) {
             const size_t nl = mg.L[l0 + k].b.nb + below(mg.L[l0 + k].b);
             v.stride = (int)nl;
             v.off_w = (int)(off + below(mg.L[l0 + k].b));
-            off += (DIM + 1) * nl;
+            off += (general ? DIM : DIM + 1) * nl;
         }
         const size_t nd2 = (size_t)s.ndense * s.ndense;
         auto whole = [](size_t n) { return (n + VL - 1) / VL * VL; };
@@ -1306,8 +1321,9 @@ void plan_small(stokes_ctx &c, MG<R> &mg) {
         }
         HIPCHK(hipMemcpyAsync(mg.tab, tab.data(), sizeof(int) * tab.size(), hipMemcpyHostToDevice, c.stream));
         HIPCHK(hipMemcpyAsync(mg.owner, owner.data(), sizeof(int4) * owner.size(), hipMemcpyHostToDevice, c.stream));
-        // slots of the image that no level owns are zero (the workspace is cleared at setup)
-        k_small_image<DIM, R><<<dim3(16, s.nl + 1), kBlock, 0, c.stream>>>(s);
+        // slots of the image that no level owns are zero (the workspace is cleared at setup); the
+        // general kernel has none
+        if (!general) k_small_image<DIM, R><<<dim3(16, s.nl + 1), kBlock, 0, c.stream>>>(s);
         HIPCHK(hipStreamSynchronize(c.stream));
         mg.small = s;
         mg.nops = (int)nops;
