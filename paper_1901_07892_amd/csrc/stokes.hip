@@ -532,15 +532,29 @@ void p_residual_restrict(stokes_ctx &c, const Level<R> &L, const Level<R> &C, co
     }
 }
 
-// Levels whose sweeps run in LDS tiles (k_p_tile): walls on every side, 2D or at most
-// 64^3 cells.  In 2D the tiles are faster than two flat colour passes a sweep at every size
-// (solves with three bodies, FP64: 512^2 2.95 -> 2.13 ms, 4096x2048 17.9 -> 11.9 ms).  In 3D
-// a tile of 8^3 cells loads 2.7 (sweep) to 5.4 times (with the restriction) its cells: up to
+// Side of a level's LDS tiles (k_p_tile), in cells.  2D: tiles of 16x16 are more blocks and
+// fewer cells a thread, tiles of 32x32 load less halo: solves of 512^2 2.14 against 2.31 ms, of
+// 1024^2 3.25 against 3.44, of 4096x2048 12.6 against 11.9 (FP32 23.4 against 20.8).
+inline int tile_side(const Box &b) { return b.dim == 3 ? 8 : (long long)b.nx * b.ny <= (1LL << 20) ? 16 : 32; }
+inline double tile_count(const Box &b) {
+    const int T = tile_side(b);
+    return std::ceil((double)b.nx / T) * std::ceil((double)b.ny / T) * (b.dim == 3 ? std::ceil((double)b.nz / T) : 1.0);
+}
+
+// Levels whose sweeps run in LDS tiles: walls on every side, 2D or at most 64^3 cells.
+// In 2D the tiles are faster than two flat colour passes a sweep (solves with three bodies,
+// FP64: 512^2 2.95 -> 2.13 ms, 4096x2048 17.9 -> 11.9 ms) unless there are many of them with
+// little in them, above all few lanes of a wavefront: 100000x2, 6250 tiles an eighth full, 83
+// against 93 ms, but 2x100000 280 / 232, 3x400000 1360 / 750, 1000000x2 in FP32 458 / 387.
+// In 3D a tile of 8^3 cells loads 2.7 (sweep) to 5.4 times (with the restriction) its cells: up to
 // 64^3 cells that is less than the launches it saves (128^3 solve, its 64^3 and 32^3 levels:
 // 4.58 -> 4.26 ms); a 96^3 level is faster with the z-marching sweep (solve 3.37 against
 // 3.63 ms).
 inline bool tiled(const Box &b) {
-    return !any_periodic(b) && (b.dim == 2 || (long long)b.nx * b.ny * b.nz <= (1LL << 18));
+    if (any_periodic(b)) return false;
+    if (b.dim == 3) return (long long)b.nx * b.ny * b.nz <= (1LL << 18);
+    const double tiles = tile_count(b), T = tile_side(b);
+    return tiles <= 4096.0 || (4.0 * b.nx >= T && 8.0 * b.nx * b.ny >= T * T * tiles);
 }
 
 template <int DIM, class R, int T, int NT, int NS, bool RESTRICT>
@@ -557,10 +571,7 @@ void p_tile(stokes_ctx &c, const Level<R> &L, const R *in, R *out, const R *r, b
             const Box &cb, R *rc) {
     if constexpr (DIM == 3)
         p_tile_launch<3, R, 8, 1024, NS, RESTRICT>(c, L, in, out, r, zero_guess, ec, cb, rc);
-    // tiles of 16x16 are more blocks and fewer cells a thread, tiles of 32x32 load less halo:
-    // solves of 512^2 2.14 against 2.31 ms, of 1024^2 3.25 against 3.44, of 4096x2048 12.6
-    // against 11.9 (FP32 23.4 against 20.8)
-    else if ((long long)L.b.nx * L.b.ny <= (1LL << 20))
+    else if (tile_side(L.b) == 16)
         p_tile_launch<2, R, 16, 384, NS, RESTRICT>(c, L, in, out, r, zero_guess, ec, cb, rc);
     else
         p_tile_launch<2, R, 32, 512, NS, RESTRICT>(c, L, in, out, r, zero_guess, ec, cb, rc);
@@ -571,12 +582,14 @@ void p_tile(stokes_ctx &c, const Level<R> &L, const R *in, R *out, const R *r, b
 // two launches); with rc the last launch also restricts the residual to it.  cur and spare
 // are swapped by every such launch.  A 3D sweep with neither ec nor rc saves one launch only
 // and takes the flat passes above 2^16 cells (forty sweeps a cycle on a coarsest level of
-// 35x95x45: solve 40.5 against 44.4 ms; of 31x45x31: 17.6 against 17.0).
+// 35x95x45: solve 40.5 against 44.4 ms; of 31x45x31: 17.6 against 17.0) and where thin tiles
+// are more than one round of blocks, 256 in FP64 and 512 in FP32 (2x100x200, 325 of them, solves:
+// FP64 47 against 56 ms, FP32 50 against 41; 4x4x8192, coarsest level of 512: 182 / 217).
 template <int DIM, class R>
 void p_tile_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, int sweeps, bool zg, const R *ec,
                    const Box *cb, R *rc) {
     const Box &C = cb ? *cb : L.b;
-    const int cells = L.b.nx * L.b.ny * L.b.nz;
+    const bool flat3 = DIM == 3 && (L.b.nx * L.b.ny * L.b.nz > (1 << 16) || tile_count(L.b) > (sizeof(R) == 8 ? 256 : 512));
     while (sweeps > 0) {
         const int n = DIM == 2 ? std::min(sweeps, 2) : 1;
         sweeps -= n;
@@ -585,7 +598,7 @@ void p_tile_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, i
             if (n == 2 && down) p_tile<2, R, 2, true>(c, L, cur, spare, r, zg, ec, C, rc);
             else if (n == 2) p_tile<2, R, 2, false>(c, L, cur, spare, r, zg, ec, C, rc);
         }
-        if (DIM == 3 && !ec && !down && cells > (1 << 16)) {
+        if (flat3 && !ec && !down) {
             p_smooth<DIM, R>(c, L, cur, r, 1, zg);
             zg = false;
             continue;
@@ -600,15 +613,14 @@ void p_tile_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, i
 
 // `sweeps` red-black Gauss-Seidel sweeps of -L_rho e = r on level L, starting from
 // *cur (zero when zg; plus the prolonged coarse correction ec of level cb when
-// ec != nullptr).  With walls on every side, 2D levels and 3D levels of at most 64^3
-// cells sweep in LDS tiles (p_tile_sweeps), larger 3D levels with the fused z-marching kernel, both from
-// *cur into *spare, after which the two pointers are swapped, so *cur always names the
-// array that holds the new iterate; periodic levels (or all with flat_only) take two
-// flat colour passes in place.
+// ec != nullptr).  Tiled levels sweep in LDS tiles (p_tile_sweeps, which has the exceptions),
+// larger 3D levels with the fused z-marching kernel, both from *cur into *spare, after which
+// the two pointers are swapped, so *cur always names the array that holds the new iterate;
+// periodic and thin 2D levels (or all with flat_only) take two flat colour passes in place.
 template <int DIM, class R>
 void p_level_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, int sweeps, bool zg, const R *ec,
                     const Box *cb, bool flat_only) {
-    if (flat_only || any_periodic(L.b)) {
+    if (flat_only || any_periodic(L.b) || (DIM == 2 && !tiled(L.b))) {
         if (ec) prolong_add<DIM, R>(c, L.b, *cb, c.opt.p_prolong, ec, cur);
         p_smooth<DIM, R>(c, L, cur, r, sweeps, zg);
     } else if (tiled(L.b)) {

@@ -226,3 +226,20 @@ def test_tiled_sweep_matches_flat_and_oracle(n, precision, lin, omega):
     e, r, ec, got = _run(prob, precision, ops, p_prolong=lin, omega=omega)
     want = _oracle(prob, precision, e, r, ec, ["sweep", "sweep_zero", "sweep_ec"], lin=bool(lin), omega=omega)
     _check(prob, precision, got, want)
+
+
+@pytest.mark.parametrize("n,precision,lin,omega", [
+    ((4, 300000, 1), 0, 1, 1.1),         # 2D, over 4096 tiles with few cells in each: flat passes
+    ((4, 300000, 1), 1, 0, 1.0),
+    ((16, 70000, 1), 0, 0, 1.1),         # over 4096 tiles as well, half full
+    ((4, 4, 4092), 0, 1, 1.1),           # 512 thin 3D tiles: two rounds of blocks in FP64, one in FP32
+    ((4, 4, 4092), 1, 1, 1.1),
+])
+def test_thin_levels_match_oracle(n, precision, lin, omega):
+    """Both sides of the rules that keep thin levels out of the tiles, with the bounds of the kernels above."""
+    prob = _rand_coeff_problem(n, 33)
+    print("thin level", n, precision, lin, omega, flush=True)
+    ops = [o for o in OPS if o[1] in (0, 1)]
+    e, r, ec, got = _run(prob, precision, ops, p_prolong=lin, omega=omega)
+    want = _oracle(prob, precision, e, r, ec, ["sweep", "sweep_zero", "sweep_ec"], lin=bool(lin), omega=omega)
+    _check(prob, precision, got, want)
