@@ -109,10 +109,10 @@ typedef struct {
                             thread per point; same result to rounding */
     int p_gamma;         /* pressure cycle: 1 V-cycle, 2 W-cycle (two coarse cycles per level) */
     int p_small;         /* 1 runs the pressure cycle from the finest level whose cycle fits in
-                            the LDS of one workgroup (3D: at most 64^3 cells, 2D: 8192; possibly
-                            the finest grid itself) down to the coarsest as one single-workgroup
-                            launch per visit (same passes as 0, results equal to rounding); 0 one
-                            launch per pass */
+                            the LDS of one workgroup (2D: at most 8192 cells, 3D: 4608, or 8192 with
+                            FP32 multigrid, 6144 with a periodic axis; possibly the finest grid
+                            itself) down to the coarsest as one single-workgroup launch per visit
+                            (same passes as 0, results equal to rounding); 0 one launch per pass */
     int p_wdepth;        /* levels that use p_gamma coarse cycles: the p_wdepth finest (0 =
                             all); coarser levels take one (a V-cycle below them) */
     int p_cycles_next;   /* pressure cycles in the later applications (>= 1), 0 = automatic:
@@ -568,32 +568,40 @@ stokes_status stokes_learned_study(stokes_ctx *ctx, const double *const rhs_u[3]
                                    int max_cycles, double *res);
 
 /* ---------------------------------------------------------------------------
- * Test hook: one kernel of the pressure multigrid on the finest level, run on
- * caller data exactly as the cycle launches it.  The operator is the pressure
+ * Test hook: kernels of the pressure multigrid on the finest level, run on
+ * caller data as the cycle launches them.  The operator is the pressure
  * Poisson operator of the projection step, -L_rho = -D beta G with beta =
  * 1/rho on interior faces and Neumann walls (Sec. 4.2.4 names the projection
  * preconditioner; the multigrid is this library's subsolve for it).
  *   STOKES_POP_SWEEP          one red-black Gauss-Seidel sweep of -L_rho e = r
  *                             (cells with i+j+k even first, then odd; relaxed
  *                             by the context's p_omega as in the cycle), in the
- *                             form the cycle uses on this level: the fused
+ *                             form a sweep of its own has on this level: the fused
  *                             z-marching kernel on 3D levels of more than 2^18
- *                             cells, the LDS-tiled kernel on smaller and on 2D
- *                             levels, two colour passes on periodic ones;
+ *                             cells, the LDS-tiled kernel on smaller 3D levels
+ *                             (without ec up to 2^16 cells only) and in 2D, two
+ *                             colour passes otherwise and on periodic or very
+ *                             thin levels;
  *   STOKES_POP_SWEEP_FLAT     the same sweep as two one-thread-per-point passes;
  *   STOKES_POP_RESTRICT       out (cells of the next-coarser level) = the mean
- *                             over the 2^d children of r - (-L_rho) e, in the
- *                             cycle's form (z-marching on 3D levels of at least
+ *                             over the 2^d children of r - (-L_rho) e, as a pass
+ *                             of its own (z-marching on 3D levels of at least
  *                             2^21 cells);
- *   STOKES_POP_RESTRICT_FLAT  the same with the one-thread-per-coarse-cell kernel.
- * e_in, r   device cell arrays (Nz, Ny, Nx) of the grid; e_in NULL starts a
- *           sweep from zero
- * ec        NULL, or (sweeps with e_in only) a device cell array of the
+ *   STOKES_POP_RESTRICT_FLAT  the same with the one-thread-per-coarse-cell kernel;
+ *   STOKES_POP_SWEEP2         two sweeps (one launch on tiled 2D levels);
+ *   STOKES_POP_SWEEP_RESTRICT, STOKES_POP_SWEEP2_RESTRICT
+ *                             the cycle's way down: one or two sweeps, then the
+ *                             mean over the children of the residual, both in the
+ *                             last launch on tiled levels.
+ * e_in, r   device cell arrays (Nz, Ny, Nx) of the grid; e_in NULL starts the
+ *           sweeps from zero
+ * ec        NULL, or (sweeps without a restriction, with e_in) a device cell array of the
  *           next-coarser level whose prolongation (piecewise constant, or
  *           trilinear with p_prolong = 1) is added to e_in before the sweep, as
  *           the cycle does after its coarse-grid correction
  * out       device cell array of the fine level (sweeps) or the next-coarser
- *           level (restriction)
+ *           level (restriction); for the way down the fine level's cells, then
+ *           the next-coarser level's
  * With FP32 multigrid the inputs are rounded to float on the way in and the
  * result widened on the way out.  Uses the context's level buffers (not
  * concurrently with a solve on the same context); blocks until done.  EINVAL for
@@ -604,7 +612,10 @@ enum {
     STOKES_POP_SWEEP = 0,
     STOKES_POP_SWEEP_FLAT = 1,
     STOKES_POP_RESTRICT = 2,
-    STOKES_POP_RESTRICT_FLAT = 3
+    STOKES_POP_RESTRICT_FLAT = 3,
+    STOKES_POP_SWEEP2 = 4,
+    STOKES_POP_SWEEP_RESTRICT = 5,
+    STOKES_POP_SWEEP2_RESTRICT = 6
 };
 stokes_status stokes_pressure_op(stokes_ctx *ctx, int op, const double *e_in, const double *r, const double *ec,
                                  double *out);

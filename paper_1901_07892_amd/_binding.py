@@ -363,6 +363,7 @@ def stokes_density_rk3(grid, dt, rho_n, u_stages, rho_out, workspace, stream=Non
 
 
 POP_SWEEP, POP_SWEEP_FLAT, POP_RESTRICT, POP_RESTRICT_FLAT = 0, 1, 2, 3
+POP_SWEEP2, POP_SWEEP_RESTRICT, POP_SWEEP2_RESTRICT = 4, 5, 6
 
 
 def stokes_pressure_op(ctx, op: int, e_in, r, ec, out) -> None:

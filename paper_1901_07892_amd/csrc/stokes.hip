@@ -674,6 +674,19 @@ R *p_small_cycles(stokes_ctx &c, MG<R> &mg, R *e, const R *r, bool zero_guess, i
     return e;
 }
 
+// The way down from level L: nu1 sweeps from *cur (as p_level_sweeps), then the residual
+// averaged into C's right-hand side.
+template <int DIM, class R>
+void p_down(stokes_ctx &c, Level<R> &L, Level<R> &C, R *&cur, R *&spare, const R *r, int nu1, bool zero_guess) {
+    if (nu1 > 0 && tiled(L.b)) {
+        p_tile_sweeps<DIM, R>(c, L, cur, spare, r, nu1, zero_guess, nullptr, &C.b, C.rp);
+        return;
+    }
+    if (zero_guess && nu1 == 0) fill<R>(c, cur - L.b.guard, L.b.stride, R(0));
+    p_level_sweeps<DIM, R>(c, L, cur, spare, r, nu1, zero_guess, nullptr, nullptr, false);
+    p_residual_restrict<DIM, R>(c, L, C, cur, r, C.rp, false);
+}
+
 // V-cycle on -L_rho e = r at level l.  Returns the array that holds the new
 // iterate: e itself, or the level's other buffer (p_level_sweeps).
 template <int DIM, class R>
@@ -691,13 +704,7 @@ R *p_vcycle(stokes_ctx &c, MG<R> &mg, int l, R *e, R *r, bool zero_guess) {
     }
     const int nu1 = p_nu_pre(c, l), nu2 = p_nu_post(c, l);
     Level<R> &C = mg.L[l + 1];
-    if (nu1 > 0 && tiled(L.b)) {
-        p_tile_sweeps<DIM, R>(c, L, cur, spare, r, nu1, zero_guess, nullptr, &C.b, C.rp);
-    } else {
-        if (zero_guess && nu1 == 0) fill<R>(c, cur - L.b.guard, L.b.stride, R(0));
-        p_level_sweeps<DIM, R>(c, L, cur, spare, r, nu1, zero_guess, nullptr, nullptr, false);
-        p_residual_restrict<DIM, R>(c, L, C, cur, r, C.rp, false);
-    }
+    p_down<DIM, R>(c, L, C, cur, spare, r, nu1, zero_guess);
     // W-cycle (p_gamma = 2): a second coarse cycle on the same coarse equation
     // (pointless above the exactly solved coarsest level)
     const int gamma = gamma_at(c, mg, l);
@@ -1940,7 +1947,9 @@ void pressure_op(stokes_ctx &c, MG<R> &mg, int op, const double *e_in, const dou
     const bool flat = op == STOKES_POP_SWEEP_FLAT || op == STOKES_POP_RESTRICT_FLAT;
     load(L.b, r_in, L.rp);
     if (e_in) load(L.b, e_in, L.ep);
-    if (op == STOKES_POP_SWEEP || op == STOKES_POP_SWEEP_FLAT) {
+    R *cur = L.ep, *spare = L.ep2;
+    const int sweeps = op == STOKES_POP_SWEEP2 || op == STOKES_POP_SWEEP2_RESTRICT ? 2 : 1;
+    if (op == STOKES_POP_SWEEP || op == STOKES_POP_SWEEP_FLAT || op == STOKES_POP_SWEEP2) {
         const R *ec = nullptr;
         const Box *cb = nullptr;
         if (ec_in) {
@@ -1949,9 +1958,13 @@ void pressure_op(stokes_ctx &c, MG<R> &mg, int op, const double *e_in, const dou
             ec = C.ep;
             cb = &C.b;
         }
-        R *cur = L.ep, *spare = L.ep2;
-        p_level_sweeps<DIM, R>(c, L, cur, spare, L.rp, 1, e_in == nullptr, ec, cb, flat);
+        p_level_sweeps<DIM, R>(c, L, cur, spare, L.rp, sweeps, e_in == nullptr, ec, cb, flat);
         store(L.b, cur, out);
+    } else if (op == STOKES_POP_SWEEP_RESTRICT || op == STOKES_POP_SWEEP2_RESTRICT) {
+        Level<R> &C = mg.L[1];
+        p_down<DIM, R>(c, L, C, cur, spare, L.rp, sweeps, e_in == nullptr);
+        store(L.b, cur, out);
+        store(C.b, C.rp, out + (size_t)L.b.nx * L.b.ny * L.b.nz);
     } else {
         Level<R> &C = mg.L[1];
         p_residual_restrict<DIM, R>(c, L, C, L.ep, L.rp, C.rp, flat);
@@ -2244,14 +2257,15 @@ stokes_status stokes_pressure_op(stokes_ctx *ctx, int op, const double *e_in, co
                                  double *out) {
     if (!ctx) return STOKES_EINVAL;
     ctx->err.clear();
-    if (op < STOKES_POP_SWEEP || op > STOKES_POP_RESTRICT_FLAT) { ctx->err = "unknown op"; return STOKES_EINVAL; }
+    if (op < STOKES_POP_SWEEP || op > STOKES_POP_SWEEP2_RESTRICT) { ctx->err = "unknown op"; return STOKES_EINVAL; }
     const bool restrict_op = op == STOKES_POP_RESTRICT || op == STOKES_POP_RESTRICT_FLAT;
-    if (!r || !out || (restrict_op && (!e_in || ec)) || (ec && !e_in)) {
+    const bool down_op = op == STOKES_POP_SWEEP_RESTRICT || op == STOKES_POP_SWEEP2_RESTRICT;
+    if (!r || !out || (restrict_op && !e_in) || ((restrict_op || down_op) && ec) || (ec && !e_in)) {
         ctx->err = "bad array pointers for this op";
         return STOKES_EINVAL;
     }
     const int nlev = ctx->opt.precision == 1 ? ctx->mgf.nlev : ctx->mgd.nlev;
-    if ((restrict_op || ec) && nlev < 2) { ctx->err = "the grid has no coarser level"; return STOKES_EINVAL; }
+    if ((restrict_op || down_op || ec) && nlev < 2) { ctx->err = "the grid has no coarser level"; return STOKES_EINVAL; }
     try {
         if (ctx->dim == 3) {
             if (ctx->opt.precision == 1) pressure_op<3, float>(*ctx, ctx->mgf, op, e_in, r, ec, out);

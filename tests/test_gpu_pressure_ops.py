@@ -243,3 +243,67 @@ def test_thin_levels_match_oracle(n, precision, lin, omega):
     e, r, ec, got = _run(prob, precision, ops, p_prolong=lin, omega=omega)
     want = _oracle(prob, precision, e, r, ec, ["sweep", "sweep_zero", "sweep_ec"], lin=bool(lin), omega=omega)
     _check(prob, precision, got, want)
+
+
+@pytest.mark.parametrize("n,precision,omega", [
+    ((14, 6, 1), 0, 1.1), ((34, 18, 1), 0, 1.0), ((142, 78, 1), 1, 1.1), ((1046, 1030, 1), 0, 1.0), ((1046, 1030, 1), 1, 1.1),
+    ((16, 70000, 1), 0, 1.1), ((4, 300000, 1), 0, 1.1), ((6, 4, 10), 0, 1.1), ((18, 26, 10), 1, 1.0), ((50, 34, 42), 0, 1.0),
+    ((50, 34, 42), 1, 1.1), ((64, 64, 64), 0, 1.1), ((64, 64, 64), 1, 1.1), ((96, 64, 50), 0, 1.1)])
+def test_way_down_matches_oracle(n, precision, omega):
+    """The cycle's way down as it is launched (one or two sweeps with the restriction in the last
+    tile launch; two sweeps in one launch in 2D; pass by pass above 64^3 cells and on thin
+    levels), from zero and from an iterate, at the edges of the tiles.  Each sweep within the
+    kernels' bound; an error d of the iterate is at most 2 dg d in the residual, dg the largest
+    diagonal, and the residual adds a bound of its own on dg max|e|."""
+    import torch
+    import paper_1901_07892_amd as S
+    prob = _rand_coeff_problem(n, 35)
+    dim, tol = prob.dim, _tol(precision)
+    beta = M.betas(dim, [np.asarray(a) for a in prob.rho_faces[:dim]])
+    e, r, _ = (_as_precision(a, precision) for a in _inputs(prob, 7))
+    if precision == 1:
+        beta = [_as_precision(b, 1) for b in beta]
+    dg = sum(2.0 * b.max() / prob.h[c] ** 2 for c, b in enumerate(beta))
+    nc = int(np.prod([v // 2 for v in n[:dim]]))
+    s = solver_for(prob, precision=precision, p_omega=omega)
+    try:
+        for op, sweeps, zero, down in ((S.POP_SWEEP2, 2, False, False), (S.POP_SWEEP2, 2, True, False),
+                                       (S.POP_SWEEP_RESTRICT, 1, False, True), (S.POP_SWEEP_RESTRICT, 1, True, True),
+                                       (S.POP_SWEEP2_RESTRICT, 2, False, True), (S.POP_SWEEP2_RESTRICT, 2, True, True)):
+            print("way down", n, "precision", precision, "op", op, "zero" if zero else "", flush=True)
+            out = torch.full((e.size + (nc if down else 0),), np.nan, dtype=torch.float64, device="cuda")
+            s.pressure_op(op, None if zero else to_dev(e), to_dev(r), None, out)
+            got = to_host(out)
+            want = np.zeros_like(e) if zero else e
+            for _ in range(sweeps):
+                want = M.rb_gs_sweep(dim, prob.h, beta, want, r, False, omega)
+            top = np.abs(want).max()
+            assert np.abs(got[:e.size].reshape(e.shape) - want).max() <= sweeps * tol * top
+            if down:
+                rc = M.residual_restrict(dim, prob.h, beta, want, r, False)
+                assert np.abs(got[e.size:].reshape(rc.shape) - rc).max() <= (2 * sweeps + 1) * dg * tol * top
+    finally:
+        s.close()
+
+
+def test_way_down_argument_errors():
+    import torch
+    import paper_1901_07892_amd as S
+    prob = W.config3(scale=8)
+    s = solver_for(prob)
+    z = torch.zeros(2 * prob.n[0] * prob.n[1] * prob.n[2], dtype=torch.float64, device="cuda")
+    try:
+        for args in [(S.POP_SWEEP2_RESTRICT + 1, z, z, None, z), (S.POP_SWEEP_RESTRICT, z, z, z, z),
+                     (S.POP_SWEEP2_RESTRICT, z, None, None, z), (S.POP_SWEEP2, None, z, z, z)]:
+            with pytest.raises(S.StokesError) as ei:
+                s.pressure_op(*args)
+            assert ei.value.status == -1
+    finally:
+        s.close()
+    s = solver_for(_rand_coeff_problem((15, 9, 1), 3))
+    try:
+        with pytest.raises(S.StokesError) as ei:
+            s.pressure_op(S.POP_SWEEP_RESTRICT, z, z, None, z)
+        assert ei.value.status == -1
+    finally:
+        s.close()
