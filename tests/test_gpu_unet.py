@@ -275,3 +275,90 @@ def test_unet_forward_gathered_levels_match_oracle(n):
     ref = OU.forward(p, f, bf16=True)
     assert np.linalg.norm(got - ref) <= 2e-2 * np.linalg.norm(ref)
     net.close()
+
+
+def _reference_gradients(p, f, target):
+    """Loss and gradient of the float64 network by autograd, rounded to BF16 where the library
+    stores an activation or the gradient of one."""
+    import torch
+
+    def bf16(x):
+        return x.float().bfloat16().double()
+
+    class Stored(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, x, value):
+            return bf16(x) if value else x.clone()
+
+        @staticmethod
+        def backward(ctx, g):
+            return bf16(g), None
+
+    q = torch.tensor(p, dtype=torch.float64, device="cuda", requires_grad=True)
+    cnt = [27 * a * b for _, a, b, _ in OU.SPEC]
+    offs = np.cumsum([0] + cnt + [b for _, _, b, _ in OU.SPEC])
+
+    def conv(l, x, skip=None):
+        m, (_, cin, cout, _) = x.shape[0], OU.SPEC[l]
+        w = q[offs[l]:offs[l + 1]].reshape(cout, 27, cin)
+        xp = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1, 1, 1))
+        y = q[offs[15 + l]:offs[16 + l]]
+        for t in range(27):
+            dz, dy, dx = t // 9, t // 3 % 3, t % 3
+            y = y + xp[dz:dz + m, dy:dy + m, dx:dx + m].reshape(-1, cin) @ w[:, t].T
+        y = y.reshape(m, m, m, cout)
+        if skip is not None:
+            y = y + skip
+        return Stored.apply(torch.relu(y), True) if l < 14 else Stored.apply(y, False)
+
+    def pool(x):
+        m = x.shape[0] // 2
+        return Stored.apply(x.reshape(m, 2, m, 2, m, 2, -1).mean((1, 3, 5)), True)
+
+    def up(x):
+        return Stored.apply(x.repeat_interleave(2, 0).repeat_interleave(2, 1).repeat_interleave(2, 2), False)
+
+    x = torch.nn.functional.pad(torch.tensor(f, dtype=torch.float64, device="cuda").permute(1, 2, 3, 0), (0, 13))
+    s0 = conv(1, conv(0, x))
+    s1 = conv(3, conv(2, pool(s0)))
+    s2 = conv(5, conv(4, pool(s1)))
+    d3 = conv(7, conv(6, pool(s2)))
+    d2 = conv(9, conv(8, up(d3), s2))
+    d1 = conv(11, conv(10, up(d2), s1))
+    y = conv(14, conv(13, conv(12, up(d1), s0)))[..., 0]
+    loss = (y - torch.tensor(target, dtype=torch.float64, device="cuda")).square().mean()
+    loss.backward()
+    return float(loss.detach()), q.grad.cpu().numpy()
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+def test_unet_layer_gradients_match_float64_autograd(n):
+    """Every layer's weight gradient, tap by tap, and bias gradient.  At n = 32 the two finest
+    levels take the matrix-core kernels, with layer 12's input read through the upsampling; at 64
+    three levels do, with those of layers 8, 10 and 12.  Bounds: the same reference with FP32
+    instead of FP64 sums differs by up to 0.023 of a layer's (weights or biases) and 0.040 of a
+    tap's L2 norm at these inputs at n = 16 and 32, since an altered rounding alters the ones
+    after it; three times that.  A tap with one wrong voxel in 16 is off by 0.25."""
+    import torch
+    net, p = _net(n, seed=5)
+    f, dev = _feats(n, 12)
+    target = np.random.default_rng(13).standard_normal((n, n, n)).astype(np.float32).astype(np.float64)
+    loss = net.train_step(dev[0], dev[1], dev[2], torch.from_numpy(target.astype(np.float32)).cuda(), 0.0)
+    g = net.get_grads().astype(np.float64)
+    net.close()
+    want_loss, want = _reference_gradients(p, f, target)
+    norm = np.linalg.norm
+    off, worst = 0, []
+    for l, (_, cin, cout, _) in enumerate(OU.SPEC):
+        a, b = (v[off:off + 27 * cin * cout].reshape(cout, 27, cin) for v in (g, want))
+        off += 27 * cin * cout
+        taps = [norm(a[:, t] - b[:, t]) / norm(b[:, t]) for t in range(27)]
+        worst.append((norm(a - b) / norm(b), max(taps)))
+    bias = []
+    for _, _, cout, _ in OU.SPEC:
+        bias.append(norm(g[off:off + cout] - want[off:off + cout]) / norm(want[off:off + cout]))
+        off += cout
+    print("n", n, "layers", ["%.1e" % w[0] for w in worst], "taps", ["%.1e" % w[1] for w in worst], "biases",
+          ["%.1e" % b for b in bias], flush=True)
+    assert abs(loss - want_loss) <= 0.01 * want_loss
+    assert max(w[0] for w in worst) <= 0.07 and max(w[1] for w in worst) <= 0.12 and max(bias) <= 0.07
