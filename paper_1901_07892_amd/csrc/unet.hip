@@ -673,14 +673,15 @@ struct stokes_unet {
 
 namespace {
 
-// activation slots
-enum { X_IN, A0, S0, P1, A1, S1, P2, A2, S2, P3, A3, D3, U2, X2, D2, U1, X1, D1, U0, X0, D0, Y16, NSLOT };
+// activation slots; the upsampled activations U0 .. U2 exist only as gradients (the layers
+// that would read them read the coarse ones)
+enum { X_IN, A0, S0, P1, A1, S1, P2, A2, S2, P3, A3, D3, U2, X2, D2, U1, X1, D1, U0, X0, D0, NSLOT };
 struct Slot {
     int level, ch;
 };
-constexpr Slot kSlot[NSLOT] = {{0, 16}, {0, 16}, {0, 16}, {1, 16}, {1, 32}, {1, 32}, {2, 32}, {2, 48},
-                               {2, 48}, {3, 48}, {3, 64}, {3, 64}, {2, 64}, {2, 48}, {2, 48}, {1, 48},
-                               {1, 32}, {1, 32}, {0, 32}, {0, 16}, {0, 16}, {0, 16}};
+constexpr Slot kSlot[NSLOT] = {{0, 16}, {0, 16}, {0, 16}, {1, 16}, {1, 32}, {1, 32}, {2, 32},
+                               {2, 48}, {2, 48}, {3, 48}, {3, 64}, {3, 64}, {2, 64}, {2, 48},
+                               {2, 48}, {1, 48}, {1, 32}, {1, 32}, {0, 32}, {0, 16}, {0, 16}};
 
 size_t carve(stokes_unet &u, char *base) {
     size_t off = 0;
@@ -710,8 +711,8 @@ size_t carve(stokes_unet &u, char *base) {
     for (int s = 0; s < NSLOT; ++s) {
         long long nl = u.n >> kSlot[s].level;
         size_t bytes = sizeof(bf16) * (size_t)(nl * nl * nl) * kSlot[s].ch;
-        u.act[s] = (bf16 *)take(bytes);
-        u.grad[s] = (bf16 *)take(bytes);
+        if (s != U0 && s != U1 && s != U2) u.act[s] = (bf16 *)take(bytes);
+        if (s != X_IN) u.grad[s] = (bf16 *)take(bytes);
     }
     long long nv = (long long)u.n * u.n * u.n;
     u.y = (float *)take(sizeof(float) * nv);

@@ -354,3 +354,16 @@ def test_binding_passes_arrays_of_the_right_size(S, monkeypatch):
                  "stokes_rigid_projection_noalloc", "stokes_wave_inflow", "stokes_density_rk3", "stokes_setup",
                  "stokes_apply", "stokes_solve", "stokes_inflow_lift"):
         assert calls.count(name) == 2, name
+
+
+def test_unet_workspace_holds_what_the_passes_use(S):
+    """At 128^3, in bytes a voxel of the finest level: 2 for each channel of the activations that a
+    layer reads (80 there, 144 on the second level, 224, 176) and of the gradients the backward pass
+    writes (96, 192, 288, 176), 36 for the prediction and its gradient; the partial sums of the largest
+    weight gradient (512 copies of 64 -> 48 channels) and the parameters (16 bytes each, 4 more
+    for the BF16 copies of a weight) come on top."""
+    acts, grads = (80 + 144 / 8 + 224 / 64 + 176 / 512), (96 + 192 / 8 + 288 / 64 + 176 / 512)
+    p = S.stokes_unet_param_count()
+    biases = 2 * (16 + 32 + 48 + 64 + 48 + 32 + 16) + 16
+    want = 128 ** 3 * (2 * (acts + grads) + 36) + 4 * 512 * 48 * 27 * 64 + 20 * p - 4 * biases
+    assert want <= S.stokes_unet_workspace_size(128) <= want + 64 * 1024
