@@ -32,8 +32,8 @@ namespace {
 // Threads of a block and z planes it marches over.  Bound by the seven output streams, which
 // run best when the blocks in flight cover few planes; but a short march loads the plane below
 // it for fewer planes, and small or 2D grids want more blocks.  From 2^21 points on in 3D 512 x 4
-// (256^3, two solids: 298 us against 321 with 256 x 8; 256x40x200: 34.8 against 36.5), below
-// and in 2D 256 x 8 (24x256x200: 25.4 against 26.4; 2048x1500: 33.7 against 45.9).
+// (two solids: 256^3 290 us against 314 with 256 x 8, 256x40x200 38.0 against 40.7), below
+// and in 2D 256 x 8 (24x256x200: 22.9 against 24.1; 2000x2000: 42.7 against 55).
 constexpr long long kCoefWide = 1LL << 21;
 
 struct CoefArgs {

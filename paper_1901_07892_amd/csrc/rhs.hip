@@ -129,9 +129,10 @@ __global__ void __launch_bounds__(kRhsBlock) k_explicit_rhs2(RhsArgs a, double *
 // The stress differences along z need the edges of the next plane, so plane k is written
 // in the step of plane k + 1.  Bound by the latency of a plane step, its loads and two
 // barriers: 250 x 190 x 131 in 315 us with loads waited for in the same step, nine
-// harmonic means per point and one 512-thread block per CU; 193 us now (3.4 TB/s).  Of
+// harmonic means per point and one 512-thread block per CU; 191 us now (3.4 TB/s), with 136
+// registers and three wavefronts per SIMD.  Of
 // the blocks tried (64 x 16, 64 x 8, 32 x 32, 32 x 16, 32 x 8, 16 x 16) the small one
-// wins although its overlap is the larger: four of them share a CU.
+// wins although its overlap is the larger: three of them share a CU.
 // The wall-normal faces beyond the last cell of a row, column or stack (i = Nx, j = Ny,
 // k = Nz) hold zero and are written by that last cell's thread.
 constexpr int kZX = 32, kZY = 8;
@@ -297,8 +298,9 @@ extern "C" stokes_status stokes_explicit_rhs(const stokes_grid *grid, const doub
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (dim == 3) {
-        // z chunks of at least 4 planes (a chunk loads two more); 250 x 190 x 131 with
-        // 1024 / 2048 / 4096 blocks aimed at: 311 / 193 / 267 us
+        // z chunks halved down to 3 or 4 planes (a chunk loads two more) while there are fewer than
+        // kRhsBlocks blocks; with 1024 / 2048 / 4096 of them aimed at: 128^3 62 / 64 / 65 us, 200^3
+        // 247 / 243 / 256, 250 x 190 x 131 207 / 183 / 198, 256^3 580 / 508 / 493, 1024 x 96 x 96 305 / 260 / 273
         const int gx = (a.nx + kOX - 1) / kOX, gy = (a.ny + kOY - 1) / kOY;
         int kc = a.nz;
         while (kc > 4 && (double)gx * gy * ((a.nz + kc - 1) / kc) < kRhsBlocks) kc = (kc + 1) / 2;

@@ -636,7 +636,7 @@ void p_level_sweeps(stokes_ctx &c, Level<R> &L, R *&cur, R *&spare, const R *r, 
 // Cells of either colour that the first level of a single-workgroup cycle may have: more
 // leave it to a launch per pass or tile and start the cycle at a coarser level, if there is one.
 // Walls: the register-resident kernel takes four cells a thread in 2D (442x66, its coarsest level
-// of 3663 a colour: 5.3 ms a step against 9.4 pass by pass) and in FP32 (24x20x20 and up, of 4800,
+// of 3663 a colour: 10.8 ms a solve against 25 pass by pass) and in FP32 (24x20x20 and up, of 4800,
 // are faster from their second level), two in FP64 in 3D.  Between those and 2304 the general
 // kernel (solves, us: 16x16x17, of 2176, 4670 against 4900 in tiles; 18x16x16, of 2304, 2040 / 2065;
 // but 20x16x16, of 2560, 950 / 900, and 19^3, of 3610, 8200 / 6250).

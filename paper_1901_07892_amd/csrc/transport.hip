@@ -167,8 +167,8 @@ __global__ void __launch_bounds__(kTrX *kTrY) k_rk3_stage2(TrGrid g, StageArgs s
 // and of the 12 arrays that a stage has to move (density, velocity, rho_n, result) each
 // plane comes from memory once: one thread per face of one component re-read the planes
 // k-2 .. k+2 of a density from beyond L2 (its five planes of every array in flight exceed
-// an XCD's 4 MB) and was bound by that: 968 us per stage at 256^3, now 538 (3.0 TB/s of
-// those 12 arrays).  174 registers, two wavefronts per SIMD; at 128 it spills (940 us).
+// an XCD's 4 MB) and was bound by that: 968 us per stage at 256^3, now 545 (3.0 TB/s of
+// those 12 arrays).  166 registers, three wavefronts per SIMD; at 128 it spills (940 us).
 // What is left is about equal parts of vector instructions (0.3 ms) and cache accesses.
 // The wall faces i = Nx, j = Ny, k = Nz hold rho_n and are written by the last cells.
 template <int TX>

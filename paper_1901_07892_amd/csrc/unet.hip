@@ -110,7 +110,7 @@ __device__ inline void conv_store(const ConvArgs &a, size_t v, int cb, f4v acc) 
 // (With the taps found per lane by division and the weights of a chunk read again from
 // LDS or the caches, 16 -> 16 channels at 64^3 took 23 us, now 15; 48 -> 48 at 16^3 27, now 9.)
 template <int CIN, int COUT>
-constexpr int conv_tiles() { return CIN == 16 ? COUT / 16 : 1; }   // at most 28 weight registers quads
+constexpr int conv_tiles() { return CIN == 16 ? COUT / 16 : 1; }   // weights: 14 NCO register quads at CIN = 16, else 27, 41, 54
 
 template <int CIN, int COUT>
 __global__ void __launch_bounds__(256) k_conv(int n, int zc, ConvArgs a) {

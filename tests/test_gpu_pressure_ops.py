@@ -1,8 +1,9 @@
 """GPU parity of the pressure-multigrid kernels, one launch at a time.
 
 Through the C-ABI test hook stokes_pressure_op, the finest-level red-black
-sweep and residual + restriction run exactly as the cycle launches them (the
-fused z-marching sweep on 3D levels of more than 2^18 cells, the z-marching
+sweep and residual + restriction run as the cycle launches them (the
+fused z-marching sweep on 3D levels of more than 2^18 cells, LDS tiles on smaller
+and 2D ones, with the restriction in the last sweep's launch; the z-marching
 residual + restriction on levels of at least 2^21 cells) and in their flat
 forms, on the workloads' own coefficients at their stated sizes (config 3's
 128^3, config 4's 1024x96x96, the 256^3 headline) and on ragged grids that
@@ -44,7 +45,8 @@ CASES = [
     ("rand_136x136x120", lambda: _rand_coeff_problem((136, 136, 120), 12)),
     # between 2^18 and 2^20 cells: the pipelined 32x16 fused sweep
     ("config5_96", lambda: W.config5(n_cells=96)),
-    # at most 2^18 cells: two flat colour passes, the prolongation folded into them
+    # at most 2^18 cells: LDS tiles with the prolongation folded in; a sweep without it takes
+    # two flat colour passes above 2^16 cells
     ("config5_64", lambda: W.config5(n_cells=64)),
     ("rand_64x48x40", lambda: _rand_coeff_problem((64, 48, 40), 14)),
     ("config2_512", lambda: W.config2()),
@@ -216,7 +218,7 @@ def test_pressure_kernels_open_top_match_oracle(name, maker):
     ((6, 4, 10), 0, 1, 1.1),             # less than one 8^3 tile along two axes
     ((18, 26, 10), 0, 0, 1.0),
     ((50, 34, 42), 1, 1, 1.1),
-    ((64, 64, 64), 0, 1, 1.1),           # 2^18 cells, the largest tiled 3D level
+    ((64, 64, 64), 0, 1, 1.1),           # 2^18 cells, the largest tiled 3D level (the sweep with ec)
 ])
 def test_tiled_sweep_matches_flat_and_oracle(n, precision, lin, omega):
     """Sizes around the tiles' edges, both prolongations, with the bounds of the kernels above."""
