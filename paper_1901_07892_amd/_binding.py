@@ -367,9 +367,10 @@ POP_SWEEP2, POP_SWEEP_RESTRICT, POP_SWEEP2_RESTRICT = 4, 5, 6
 
 
 def stokes_pressure_op(ctx, op: int, e_in, r, ec, out) -> None:
-    """One pressure-multigrid kernel of the finest level on caller cell arrays
+    """Pressure-multigrid kernels of the finest level on caller cell arrays
     (device float64 tensors; ``e_in`` None = from zero, ``ec`` None = no coarse
-    correction).  Blocks until done."""
+    correction; ``out`` of POP_SWEEP_RESTRICT and POP_SWEEP2_RESTRICT holds the
+    fine cells, then the next-coarser level's).  Blocks until done."""
     L = load_library()
     st = L.stokes_pressure_op(ctx, int(op), _ptr(e_in), _ptr(r), _ptr(ec), _ptr(out))
     if st != 0:
